@@ -13,19 +13,17 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cmath>
 #include <string>
 #include <type_traits>
 
 #include "hb_tile.h"
+#include "hb_tile_shape.h"
 
 namespace hb {
 namespace {
 
-constexpr int kThreads = 1024;
+constexpr int kThreads = kTileThreads, kStage = kTileStage;
 constexpr int kWaves = kThreads / 64;
-constexpr int kStage = 4;              // 16-byte pieces of a chunk per thread: chunks of up to 64 KiB
-constexpr int kChunkMax = kStage * kThreads * 16;
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -284,9 +282,9 @@ __device__ __forceinline__ void flush_slots(const TileArgs &a, uint32_t stage, u
     int id[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const uint32_t slot = *(lds_u16 *)(uintptr_t)(stage + (k4 + j) * sstride + 2u * r);
-      id[j] = a.id_base + (int)slot;
-      if (a.id_base < 0) id[j] = k4 + j < st ? a.leaf_id[(size_t)(t0 + k4 + j) * a.leaf_slots + slot] : 0;
+      const int k = tile_flush_tree(k4 + j, st);
+      const uint32_t slot = *(lds_u16 *)(uintptr_t)(stage + k * sstride + 2u * r);
+      id[j] = a.id_base < 0 ? a.leaf_id[(size_t)(t0 + k) * a.leaf_slots + slot] : a.id_base + (int)slot;
     }
     int32_t *dst = a.leaf_ids + (r0 + r) * T + t0 + k4;
     if (a.ids_vec && k4 + 4 <= st) {
@@ -372,7 +370,7 @@ __global__ __launch_bounds__(kThreads) void tile_kernel(TileArgs a) {
       }
     }
   };
-  const uint32_t sstride = 2u * (uint32_t)R + 4u;
+  const uint32_t sstride = tile_slot_stride(R);
   const uint32_t stage0 = lds + (uint32_t)a.stage_off;
   const int st = a.st_chunks * a.nt;
   const uint32_t stage_bytes = (uint32_t)st * sstride;
@@ -581,88 +579,6 @@ TileFn pick(int km, bool vec, int ilp) {
 
 }  // namespace
 
-namespace {
-
-// A launch shape: R rows per workgroup, nt trees per chunk, ilp trees a wave
-// walks together (nt is a multiple of ilp for every wave group).
-struct Shape {
-  int rows = 0;  // 0: does not fit
-  int split = 0, parts = 1;  // chunks per workgroup of a tree split (0: all), workgroups per row tile
-  int nt = 0, ilp = 0, bufs = 0, st_chunks = 0, buf_off = 0, stage_off = 0, lds = 0;
-  double cost = 0;
-};
-
-// The shape of the least estimated time in clocks: rounds of workgroups over
-// the CUs, each of
-//   walk    a wave-level step (node and feature read, four vector
-//           instructions) every 7 clocks or a little more where enough are in
-//           flight, else the 260 clocks of the dependent reads over the
-//           16 ilp in flight;
-//   chunks  1,300 clocks to hand a chunk over, and its bytes at 40 a clock;
-//   ranks   0.22 clocks per threshold staged, 11 per search step of 64 rows.
-// The constants are fitted to forced shapes on 28 to 300 columns, 60K to 1M
-// rows; the shapes it takes are the fastest measured or within 10% of it.
-//
-// With ws_bytes a batch too small to give every CU a row tile may also divide
-// the chunks of a tile among workgroups; each adds a tile load (2,000 clocks and
-// 3 per value of 64 rows), and the second kernel that adds the parts takes
-// about 10,000.
-Shape best_shape(const EnsembleDev &e, const TileDev &t, int levels, int64_t n_rows, bool ids, int64_t ws_bytes,
-                 int lds_max, int cus) {
-  Shape best;
-  if (!t.recs) return best;
-  const bool rank = t.thr != nullptr;
-  for (int lg = rank ? 7 : 6; lg <= 10; ++lg) {
-    const int R = 1 << lg, G = kThreads / R;
-    const int64_t buf = ((int64_t)e.n_cols * R * (rank ? 2 : 4) + 15) / 16 * 16;
-    for (int bufs = 2; bufs >= 1; --bufs)
-      for (int ilp : {1, 2, 3, 4, 8})
-        for (int nt = G * ilp; nt <= (ids ? 32 : 64); nt += G * ilp) {
-          if ((int64_t)nt * t.tree_bytes > kChunkMax) break;
-          // leaf ids are written for up to 32 trees at a time (a 128-byte line per row)
-          const int64_t slots = ids ? 2LL * nt * (2 * R + 4) : 0, stage = buf + (int64_t)bufs * nt * t.tree_bytes;
-          if (stage + slots > lds_max) break;
-          int m = 1;
-          while (ids && 2 * m * nt <= 32 && stage + 2 * m * slots <= lds_max) m *= 2;
-          const double tiles = (double)((n_rows + R - 1) / R), chunks = std::ceil((double)e.n_trees / nt);
-          const double bytes = (double)nt * t.tree_bytes;
-          const double walk = (double)nt * levels * (R / 64) * std::max(7.0 + 1.0 / ilp, 260.0 / (16 * ilp));
-          const double hand = 1300.0 + bytes / 40.0 + (bufs == 1 ? 700.0 + bytes / 64.0 : 0.0);
-          const double ranks = rank ? 0.22 * t.n_thr + 11.0 * t.search_steps * (R / 64) : 0.0;
-          const double load = ws_bytes ? 2000.0 + 3.0 * e.n_cols * (R / 64) + ranks : ranks;
-          double cost = std::ceil(tiles / cus) * (chunks * (walk + hand) + load);
-          int split = 0, parts = 1;
-          if (ws_bytes && tiles < cus)
-            for (int per = 1; per < (int)chunks; ++per) {
-              const int p = ((int)chunks + per - 1) / per;
-              if ((int64_t)p * n_rows * e.n_outputs * 8 > ws_bytes) continue;
-              const double c = std::ceil(tiles * p / cus) * (per * (walk + hand) + load) + 10000.0;
-              if (c < cost) {
-                cost = c;
-                split = per;
-                parts = p;
-              }
-            }
-          if (best.rows && cost >= best.cost * 0.999) continue;
-          best.cost = cost;
-          best.split = split;
-          best.parts = parts;
-          best.rows = R;
-          best.nt = nt;
-          best.ilp = ilp;
-          best.bufs = bufs;
-          best.st_chunks = m;
-          best.buf_off = (int)buf;
-          best.stage_off = (int)stage;
-          // (thresholds pass through all of the LDS the tile leaves; the group sums take 8 K bytes per thread)
-          best.lds = rank ? lds_max : (int)std::max<int64_t>(stage + m * slots, (int64_t)kThreads * e.n_outputs * 8);
-        }
-  }
-  return best;
-}
-
-}  // namespace
-
 int launch_tile(bool perfect, const EnsembleDev &e, const TileDev &tile, const TileDev *rank, const int32_t *leaf_id,
                 int leaf_slots, int levels, const int32_t *tree_depth, const float *X, int64_t n_rows, float *scores,
                 int32_t *leaf_ids, const Launch &ws, hipStream_t stream, std::string *err) {
@@ -677,9 +593,14 @@ int launch_tile(bool perfect, const EnsembleDev &e, const TileDev &tile, const T
   if ((!tile.recs && !(rank && rank->recs)) || (!ws_bytes && n_rows < (int64_t)kTileMinRowsPerCu * cus)) return 1;
   if ((int64_t)kThreads * e.n_outputs * 8 > lds_max) return 1;
   const TileDev *tp = &tile;
-  Shape p = best_shape(e, tile, levels, n_rows, leaf_ids != nullptr, ws_bytes, lds_max, cus);
+  auto shape = [&](const TileDev &t) {
+    if (!t.recs) return TileShape{};
+    const TileSpec spec{e.n_trees, e.n_cols, e.n_outputs, levels, t.tree_bytes, t.thr != nullptr, t.n_thr, t.search_steps};
+    return best_shape(spec, n_rows, leaf_ids != nullptr, ws_bytes, lds_max, cus);
+  };
+  TileShape p = shape(tile);
   if (rank) {
-    const Shape q = best_shape(e, *rank, levels, n_rows, leaf_ids != nullptr, ws_bytes, lds_max, cus);
+    const TileShape q = shape(*rank);
     if (q.rows && (!p.rows || q.cost < p.cost)) {
       p = q;
       tp = rank;

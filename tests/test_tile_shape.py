@@ -1,0 +1,93 @@
+"""Launch shapes of the tile kernel (csrc/hb_tile_shape.h), compiled for the
+host: what the kernel derives from a shape stays inside its LDS."""
+import ctypes
+import itertools
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2010_04804_amd", "csrc")
+LDS, CUS = 160 * 1024, 256
+
+SOURCE = r"""
+#include "hb_tile_shape.h"
+extern "C" {
+void shape(int n_trees, int n_cols, int n_outputs, int levels, int tree_bytes, int rank, int n_thr, int steps,
+           long long n_rows, int ids, long long ws_bytes, int lds_max, int cus, int *out) {
+  const hb::TileSpec t{n_trees, n_cols, n_outputs, levels, tree_bytes, rank != 0, n_thr, steps};
+  const hb::TileShape s = hb::best_shape(t, n_rows, ids != 0, ws_bytes, lds_max, cus);
+  const int v[] = {s.rows, s.split, s.parts, s.nt, s.ilp, s.bufs, s.st_chunks, s.buf_off, s.stage_off, s.lds};
+  for (int i = 0; i < 10; ++i) out[i] = v[i];
+}
+int flush_tree(int k, int st) { return hb::tile_flush_tree(k, st); }
+int slot_stride(int rows) { return (int)hb::tile_slot_stride(rows); }
+}
+"""
+FIELDS = ["rows", "split", "parts", "nt", "ilp", "bufs", "st_chunks", "buf_off", "stage_off", "lds"]
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("tile_shape")
+    (d / "shape.cpp").write_text(SOURCE)
+    subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, "-o", str(d / "shape.so"),
+                    str(d / "shape.cpp")], check=True)
+    return ctypes.CDLL(str(d / "shape.so"))
+
+
+# model kind: levels, bytes per tree, rank tile, thresholds per (column, tree)
+TREES = {"perfect5": (5, 256, False, 0), "perfect8": (8, 2048, False, 0), "perfect9": (9, 4096, False, 0),
+         "perfect11": (11, 16384, False, 0), "rank8": (8, 1024, True, 255), "rank12": (12, 16384, True, 4095),
+         "leafwise31": (12, 496, False, 0), "leafwise256": (12, 4096, False, 0)}
+
+
+def spec(kind, T, F, K):
+    levels, tree_bytes, rank, per_tree = TREES[kind]
+    n_thr = T * per_tree if rank else 0
+    steps = F * max(1, (max(n_thr // F, 1)).bit_length()) if rank else 0
+    return (T, F, K, levels, tree_bytes, int(rank), n_thr, steps)
+
+
+def best(lib, kind, T, F, K, n, ids, ws):
+    out = (ctypes.c_int * 10)()
+    lib.shape(*spec(kind, T, F, K), ctypes.c_longlong(n), int(ids), ctypes.c_longlong(ws), LDS, CUS, out)
+    return dict(zip(FIELDS, out))
+
+
+CASES = [(k, T, F, K, n, ws) for k, T, F, K, (n, ws) in itertools.product(
+    TREES, (4, 60, 100, 300, 800, 3500), (10, 28, 60, 130, 300), (1, 2, 7),
+    ((1100, 1 << 30), (8000, 1 << 30), (16_000, 1 << 20), (50_021, 0), (100_003, 0), (1_000_000, 0)))]
+
+
+def flush_sizes(s, T):
+    """Trees per flush: full groups of chunks, and the groups that end a
+    workgroup's part of the trees."""
+    chunks = -(-T // s["nt"])
+    per = s["split"] or chunks
+    out = set()
+    for begin in range(0, chunks, per):
+        end, c = min(begin + per, chunks), begin
+        while c < end:
+            m = min(s["st_chunks"], end - c)
+            out.add((c * s["nt"], min(m * s["nt"], T - c * s["nt"])))
+            c += m
+    return out
+
+
+def test_leaf_id_flush_reads_its_staging(lib):
+    """Each lane of a flush takes four consecutive trees: the slots it reads
+    are staged ones (the second staging buffer ends the kernel's LDS)."""
+    for kind, T, F, K, n, ws in CASES:
+        s = best(lib, kind, T, F, K, n, True, ws)
+        if not s["rows"]:
+            continue
+        st = s["st_chunks"] * s["nt"]
+        stride = lib.slot_stride(s["rows"])
+        label = (kind, T, F, K, n, s)
+        assert st <= 32 and s["lds"] <= LDS, label
+        for t0, m in flush_sizes(s, T):
+            assert 1 <= m <= st, label
+            last = max(lib.flush_tree(4 * lane + j, m) for lane in range(8) for j in range(4) if 4 * lane < m)
+            end = s["stage_off"] + st * stride + last * stride + 2 * (s["rows"] - 1) + 2
+            assert last < m and end <= s["lds"], label
