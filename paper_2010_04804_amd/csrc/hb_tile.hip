@@ -27,6 +27,7 @@ constexpr int kWaves = kThreads / 64;
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef int ids4 __attribute__((ext_vector_type(4), aligned(kTileIdStoreAlign)));
 typedef __attribute__((address_space(3))) const uint32_t lds_u32;
 typedef __attribute__((address_space(3))) const uint64_t lds_u64;
 typedef __attribute__((address_space(3))) const float lds_f32;
@@ -67,7 +68,7 @@ struct TileArgs {
   int32_t buf_off, stage_off;  // LDS byte offsets of the chunk buffers and the leaf-slot staging
   int32_t scratch;           // RANK: floats of LDS from buf_off on, for the thresholds
   int32_t st_chunks;         // chunks per leaf-id flush
-  int32_t ids_vec;           // leaf ids may be stored 16 bytes at a time
+  int32_t ids_vec;           // leaf-id rows start 16-byte aligned: stored 16 bytes at a time
 };
 
 // LDS byte offset of row r within a column of the tile. 16-bit tiles put the
@@ -279,7 +280,7 @@ __device__ __forceinline__ void flush_slots(const TileArgs &a, uint32_t stage, u
   for (int rb = wave; rb < (R >> 3); rb += kWaves) {
     const int r = 8 * rb + (lane >> 3);
     if (k4 >= st || r0 + r >= a.n_rows) continue;
-    int id[4];
+    ids4 id;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int k = tile_flush_tree(k4 + j, st);
@@ -288,7 +289,7 @@ __device__ __forceinline__ void flush_slots(const TileArgs &a, uint32_t stage, u
     }
     int32_t *dst = a.leaf_ids + (r0 + r) * T + t0 + k4;
     if (a.ids_vec && k4 + 4 <= st) {
-      *reinterpret_cast<int4 *>(dst) = make_int4(id[0], id[1], id[2], id[3]);
+      *reinterpret_cast<ids4 *>(dst) = id;
     } else {
 #pragma unroll
       for (int j = 0; j < 4; ++j)

@@ -43,6 +43,10 @@ HB_HOST_DEVICE constexpr uint32_t tile_slot_stride(int rows) { return 2u * (uint
 // The staged tree read for place k of a flush of st trees: the places a lane
 // has beyond the last tree read that tree's slot again (and store nothing).
 HB_HOST_DEVICE constexpr int tile_flush_tree(int k, int st) { return k < st ? k : st - 1; }
+// A flush starts at a multiple of nt trees, which need not be one of four: the
+// 16-byte stores are declared with the alignment of an id (the hardware takes
+// global stores of any size at four bytes).
+constexpr int kTileIdStoreAlign = 4;
 
 // The shape of the least estimated time in clocks: rounds of workgroups over
 // the CUs, each of

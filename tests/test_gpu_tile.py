@@ -145,6 +145,32 @@ def test_tile_tree_split(kind, size, F, T, K, ld, n):
     h.close()
 
 
+@pytest.mark.parametrize("kind,size,F,T,ld,n,workspace", [
+    ("perfect", 9, 60, 100, 2, 50_003, False),      # chunks of 6 trees, one per flush
+    ("leafwise", 256, 10, 800, 1, 8_000, True)])    # tree split in parts of 27 trees, chunks of 9
+def test_tile_leaf_ids_start_at_any_tree(kind, size, F, T, ld, n, workspace):
+    """Leaf-id rows 16-byte aligned (T a multiple of four) and flushes that
+    start at no multiple of four trees and end on a lane's first or second
+    one: every id is written, and nothing around the output."""
+    m = _forest(kind, size, F, T, ld, ld, seed=size + T)
+    strategy = "ptt" if kind == "perfect" else "tt"
+    h = hb.compile(m, strategy=strategy, device=0)
+    X = np.random.Generator(np.random.PCG64(n)).standard_normal((n, F)).astype(np.float32)
+    Xd = torch.from_numpy(X).cuda()
+    nws = hb.workspace_bytes(h, n, strategy) if workspace else 0
+    say("tile ids", kind, size, F, T, ld, n, nws)
+    buf = torch.full((n * T + 8,), -7, dtype=torch.int32, device="cuda")
+    sc = torch.empty((n, max(1, ld)), dtype=torch.float32, device="cuda")
+    ws = torch.empty(max(nws, 8), dtype=torch.uint8, device="cuda")
+    hb.predict_ptr(h, Xd.data_ptr(), n, sc.data_ptr(), buf.data_ptr() + 16, strategy,
+                   torch.cuda.current_stream().cuda_stream, ws.data_ptr() if nws else None, nws)
+    torch.cuda.synchronize()
+    b = buf.cpu().numpy()
+    assert np.all(b[:4] == -7) and np.all(b[4 + n * T:] == -7)
+    check(m, X, sc.cpu().numpy(), b[4:4 + n * T].reshape(n, T), f"tile ids {kind}{size} T{T} n{n}")
+    h.close()
+
+
 @pytest.mark.parametrize("T,K,ld,n", [(1, 1, 1, 32_768), (3, 1, 1, 32_769), (5, 2, 1, 32_895), (9, 3, 3, 33_000),
                                       (4, 16, 1, 32_801)])
 def test_gemm_block_kernel(T, K, ld, n):

@@ -1,5 +1,6 @@
 """Launch shapes of the tile kernel (csrc/hb_tile_shape.h), compiled for the
-host: what the kernel derives from a shape stays inside its LDS."""
+host: what the kernel derives from a shape stays inside its LDS and keeps the
+alignment that its stores are declared with."""
 import ctypes
 import itertools
 import os
@@ -22,6 +23,7 @@ void shape(int n_trees, int n_cols, int n_outputs, int levels, int tree_bytes, i
 }
 int flush_tree(int k, int st) { return hb::tile_flush_tree(k, st); }
 int slot_stride(int rows) { return (int)hb::tile_slot_stride(rows); }
+int store_align() { return hb::kTileIdStoreAlign; }
 }
 """
 FIELDS = ["rows", "split", "parts", "nt", "ilp", "bufs", "st_chunks", "buf_off", "stage_off", "lds"]
@@ -75,9 +77,12 @@ def flush_sizes(s, T):
     return out
 
 
-def test_leaf_id_flush_reads_its_staging(lib):
+def test_leaf_id_flush_reads_its_staging_and_stores_aligned(lib):
     """Each lane of a flush takes four consecutive trees: the slots it reads
-    are staged ones (the second staging buffer ends the kernel's LDS)."""
+    are staged ones (the second staging buffer ends the kernel's LDS), and its
+    16-byte stores begin at ids that the declared alignment allows. Many
+    shapes have flushes that start at no multiple of four trees."""
+    align, odd = lib.store_align(), 0
     for kind, T, F, K, n, ws in CASES:
         s = best(lib, kind, T, F, K, n, True, ws)
         if not s["rows"]:
@@ -91,3 +96,7 @@ def test_leaf_id_flush_reads_its_staging(lib):
             last = max(lib.flush_tree(4 * lane + j, m) for lane in range(8) for j in range(4) if 4 * lane < m)
             end = s["stage_off"] + st * stride + last * stride + 2 * (s["rows"] - 1) + 2
             assert last < m and end <= s["lds"], label
+            if T % 4 == 0:  # rows of the output are 16-byte aligned
+                odd += t0 % 4 != 0
+                assert 4 * t0 % align == 0, label
+    assert odd > 0  # such shapes are reached
