@@ -34,6 +34,7 @@ struct TileShape {
   int split = 0, parts = 1;  // chunks per workgroup of a tree split (0: all), workgroups per row tile
   int nt = 0, ilp = 0, bufs = 0, st_chunks = 0, buf_off = 0, stage_off = 0, lds = 0;
   double cost = 0;
+  int tried = 0;  // estimates made to find it
 };
 
 // Leaf ids pass through LDS as 16-bit slots: st trees' columns of the
@@ -63,40 +64,71 @@ constexpr int kTileIdStoreAlign = 4;
 // the chunks of a tile among workgroups; each adds a tile load (2,000 clocks and
 // 3 per value of 64 rows), and the second kernel that adds the parts takes
 // about 10,000.
+//
+// The search runs on every call, so its cost must not grow with the trees:
+//   * a split of k rounds of workgroups is cheapest with the fewest chunks per
+//     workgroup that k rounds hold, so only those are tried, round by round,
+//     until the rounds' loads alone exceed what is gained;
+//   * a chunk size is left out where its bytes, its walks and T / nt hand-overs
+//     (ragged chunks only add to them) already cost more than the best shape.
+// Both leave the result as trying everything gives it (time on one host core: 500
+// depth-8 trees with 2-vectors, 10,000 rows 55 us, now 2.2; 3,500 trees of 31
+// leaves, 7 classes, 4,000 rows 503, now 3.3).
 inline TileShape best_shape(const TileSpec &t, int64_t n_rows, bool ids, int64_t ws_bytes, int lds_max, int cus) {
   TileShape best;
   const bool rank = t.rank;
+  const int64_t max_parts = ws_bytes / (n_rows * t.n_outputs * 8);
   for (int lg = rank ? 7 : 6; lg <= 10; ++lg) {
     const int R = 1 << lg, G = kTileThreads / R;
     const int64_t buf = ((int64_t)t.n_cols * R * (rank ? 2 : 4) + 15) / 16 * 16;
-    for (int bufs = 2; bufs >= 1; --bufs)
-      for (int ilp : {1, 2, 3, 4, 8})
-        for (int nt = G * ilp; nt <= (ids ? 32 : 64); nt += G * ilp) {
-          if ((int64_t)nt * t.tree_bytes > kTileChunkMax) break;
-          // leaf ids are written for up to 32 trees at a time (a 128-byte line per row)
-          const int64_t slots = ids ? 2LL * nt * (2 * R + 4) : 0, stage = buf + (int64_t)bufs * nt * t.tree_bytes;
-          if (stage + slots > lds_max) break;
+    const int64_t row_tiles = (n_rows + R - 1) / R;
+    const double tiles = (double)row_tiles, rounds = std::ceil(tiles / cus), share = tiles / cus;
+    const bool may_split = ws_bytes && row_tiles < cus;
+    const double ranks = rank ? 0.22 * t.n_thr + 11.0 * t.search_steps * (R / 64) : 0.0;
+    const double load = ws_bytes ? 2000.0 + 3.0 * t.n_cols * (R / 64) + ranks : ranks;
+    // LDS of a tree's id slots: ids are written for up to 32 trees at a time (a 128-byte line per row)
+    const int64_t slot = ids ? 2LL * tile_slot_stride(R) : 0;
+    for (int bufs = 2; bufs >= 1; --bufs) {
+      const int64_t room = buf <= lds_max ? (lds_max - buf) / (bufs * (int64_t)t.tree_bytes + slot) : 0;
+      const int nt_max = (int)std::min({(int64_t)(ids ? 32 : 64), room, (int64_t)kTileChunkMax / t.tree_bytes});
+      for (int ilp : {1, 2, 3, 4, 8}) {
+        const double step = std::max(7.0 + 1.0 / ilp, 260.0 / (16 * ilp));
+        const double tree = t.levels * (R / 64) * step + t.tree_bytes / 40.0 + (bufs == 1 ? t.tree_bytes / 64.0 : 0.0);
+        for (int nt = G * ilp; nt <= nt_max; nt += G * ilp) {
+          const double least = t.n_trees * (tree + (bufs == 1 ? 2000.0 : 1300.0) / nt);
+          const double bound = may_split ? load + std::min(least, share * least + 10000.0) : rounds * (least + load);
+          if (best.rows && bound >= best.cost) continue;  // (a shape is taken for 0.1% less, far above rounding)
+          ++best.tried;
+          const int n_chunks = (t.n_trees + nt - 1) / nt;
+          const double chunks = (double)n_chunks;
+          const int64_t slots = nt * slot, stage = buf + (int64_t)bufs * nt * t.tree_bytes;
           int m = 1;
           while (ids && 2 * m * nt <= 32 && stage + 2 * m * slots <= lds_max) m *= 2;
-          const double tiles = (double)((n_rows + R - 1) / R), chunks = std::ceil((double)t.n_trees / nt);
           const double bytes = (double)nt * t.tree_bytes;
-          const double walk = (double)nt * t.levels * (R / 64) * std::max(7.0 + 1.0 / ilp, 260.0 / (16 * ilp));
+          const double walk = (double)nt * t.levels * (R / 64) * step;
           const double hand = 1300.0 + bytes / 40.0 + (bufs == 1 ? 700.0 + bytes / 64.0 : 0.0);
-          const double ranks = rank ? 0.22 * t.n_thr + 11.0 * t.search_steps * (R / 64) : 0.0;
-          const double load = ws_bytes ? 2000.0 + 3.0 * t.n_cols * (R / 64) + ranks : ranks;
-          double cost = std::ceil(tiles / cus) * (chunks * (walk + hand) + load);
+          double cost = rounds * (chunks * (walk + hand) + load);
           int split = 0, parts = 1;
-          if (ws_bytes && tiles < cus)
-            for (int per = 1; per < (int)chunks; ++per) {
-              const int p = ((int)chunks + per - 1) / per;
-              if ((int64_t)p * n_rows * t.n_outputs * 8 > ws_bytes) continue;
-              const double c = std::ceil(tiles * p / cus) * (per * (walk + hand) + load) + 10000.0;
-              if (c < cost) {
-                cost = c;
-                split = per;
-                parts = p;
+          if (may_split && max_parts > 1) {
+            const int least_per = (int)((n_chunks + max_parts - 1) / max_parts);
+            for (int64_t k = 1;; ++k) {
+              const int64_t most = k * cus / row_tiles;  // parts that k rounds hold (two at least)
+              const int per = std::max(most > 1 ? (int)((n_chunks + most - 1) / most) : n_chunks, least_per);
+              if (per < n_chunks) {
+                ++best.tried;
+                const int p = (n_chunks + per - 1) / per;
+                const double c = std::ceil(tiles * p / cus) * (per * (walk + hand) + load) + 10000.0;
+                if (c < cost || (c == cost && per < split)) {
+                  cost = c;
+                  split = per;
+                  parts = p;
+                }
               }
+              // later rounds: the walks' share, and one more load each
+              const double later = share * chunks * (walk + hand) + (k + 1) * load + 10000.0;
+              if (per == 1 || per == least_per || later > (best.rows ? std::min(cost, best.cost) : cost)) break;
             }
+          }
           if (best.rows && cost >= best.cost * 0.999) continue;
           best.cost = cost;
           best.split = split;
@@ -111,6 +143,8 @@ inline TileShape best_shape(const TileSpec &t, int64_t n_rows, bool ids, int64_t
           // (thresholds pass through all of the LDS the tile leaves; the group sums take 8 K bytes per thread)
           best.lds = rank ? lds_max : (int)std::max<int64_t>(stage + m * slots, (int64_t)kTileThreads * t.n_outputs * 8);
         }
+      }
+    }
   }
   return best;
 }

@@ -1,8 +1,10 @@
 """Launch shapes of the tile kernel (csrc/hb_tile_shape.h), compiled for the
 host: what the kernel derives from a shape stays inside its LDS and keeps the
-alignment that its stores are declared with."""
+alignment that its stores are declared with, and the search that every call
+makes finds what trying everything finds."""
 import ctypes
 import itertools
+import math
 import os
 import subprocess
 
@@ -18,15 +20,15 @@ void shape(int n_trees, int n_cols, int n_outputs, int levels, int tree_bytes, i
            long long n_rows, int ids, long long ws_bytes, int lds_max, int cus, int *out) {
   const hb::TileSpec t{n_trees, n_cols, n_outputs, levels, tree_bytes, rank != 0, n_thr, steps};
   const hb::TileShape s = hb::best_shape(t, n_rows, ids != 0, ws_bytes, lds_max, cus);
-  const int v[] = {s.rows, s.split, s.parts, s.nt, s.ilp, s.bufs, s.st_chunks, s.buf_off, s.stage_off, s.lds};
-  for (int i = 0; i < 10; ++i) out[i] = v[i];
+  const int v[] = {s.rows, s.split, s.parts, s.nt, s.ilp, s.bufs, s.st_chunks, s.buf_off, s.stage_off, s.lds, s.tried};
+  for (int i = 0; i < 11; ++i) out[i] = v[i];
 }
 int flush_tree(int k, int st) { return hb::tile_flush_tree(k, st); }
 int slot_stride(int rows) { return (int)hb::tile_slot_stride(rows); }
 int store_align() { return hb::kTileIdStoreAlign; }
 }
 """
-FIELDS = ["rows", "split", "parts", "nt", "ilp", "bufs", "st_chunks", "buf_off", "stage_off", "lds"]
+FIELDS = ["rows", "split", "parts", "nt", "ilp", "bufs", "st_chunks", "buf_off", "stage_off", "lds", "tried"]
 
 
 @pytest.fixture(scope="module")
@@ -52,7 +54,7 @@ def spec(kind, T, F, K):
 
 
 def best(lib, kind, T, F, K, n, ids, ws):
-    out = (ctypes.c_int * 10)()
+    out = (ctypes.c_int * 11)()
     lib.shape(*spec(kind, T, F, K), ctypes.c_longlong(n), int(ids), ctypes.c_longlong(ws), LDS, CUS, out)
     return dict(zip(FIELDS, out))
 
@@ -100,3 +102,51 @@ def test_leaf_id_flush_reads_its_staging_and_stores_aligned(lib):
                 odd += t0 % 4 != 0
                 assert 4 * t0 % align == 0, label
     assert odd > 0  # such shapes are reached
+
+
+def everything(kind, T, F, K, n, ids, ws):
+    """The shape of the least estimated time, every chunk size and every split tried."""
+    T, F, K, levels, tb, rank, n_thr, steps = spec(kind, T, F, K)
+    best, least = None, 0.0
+    for lg in range(7 if rank else 6, 11):
+        R, G = 1 << lg, 1024 >> lg
+        rw, buf = R // 64, -(-F * R * (2 if rank else 4) // 16) * 16
+        tiles = -(-n // R)
+        ranks = 0.22 * n_thr + 11.0 * steps * rw if rank else 0.0
+        load = 2000.0 + 3.0 * F * rw + ranks if ws else ranks
+        for bufs, ilp in itertools.product((2, 1), (1, 2, 3, 4, 8)):
+            for nt in range(G * ilp, (32 if ids else 64) + 1, G * ilp):
+                stage = buf + bufs * nt * tb
+                if nt * tb > 65536 or stage + (2 * nt * (2 * R + 4) if ids else 0) > LDS:
+                    break
+                chunks = -(-T // nt)
+                walk = nt * levels * rw * max(7.0 + 1.0 / ilp, 260.0 / (16 * ilp))
+                hand = 1300.0 + nt * tb / 40.0 + (700.0 + nt * tb / 64.0 if bufs == 1 else 0.0)
+                cost, split, parts = -(-tiles // CUS) * (chunks * (walk + hand) + load), 0, 1
+                for per in range(1, chunks if ws and tiles < CUS else 1):
+                    p = -(-chunks // per)
+                    if p * n * K * 8 <= ws:
+                        c = math.ceil(tiles * p / CUS) * (per * (walk + hand) + load) + 10000.0
+                        if c < cost:
+                            cost, split, parts = c, per, p
+                if best is None or cost < least * 0.999:
+                    best, least = (R, split, parts, nt, ilp, bufs), cost
+    return best
+
+
+def test_search_finds_the_shape_and_stays_short(lib):
+    """Every call searches its shape: the search is exact, and the estimates it
+    makes do not grow with the trees (trying everything takes about 30 a tree)."""
+    keys = ("rows", "split", "parts", "nt", "ilp", "bufs")
+    for kind, T, F, K, n, ids, ws in [
+            (k, T, F, K, n, ids, ws) for k, (T, F, K), (n, ws), ids in itertools.product(
+                TREES, ((1, 5, 1), (37, 60, 2), (100, 130, 1), (500, 28, 7)),
+                ((1025, 1 << 30), (4000, 1 << 16), (8000, 32 << 20), (16_384, 1 << 30), (50_021, 0), (300_007, 0)),
+                (False, True))]:
+        s = best(lib, kind, T, F, K, n, ids, ws)
+        want = everything(kind, T, F, K, n, ids, ws)
+        assert want == (tuple(s[k] for k in keys) if s["rows"] else None), (kind, T, F, K, n, ids, ws)
+    for kind, T, F, n, ids in itertools.product(TREES, (1, 100, 3500, 20_000), (1, 28, 130),
+                                                (1025, 2000, 4000, 8000, 16_384, 1_000_000), (False, True)):
+        s = best(lib, kind, T, F, 1, n, ids, (1 << 30) if n <= 16_384 else 0)
+        assert s["tried"] <= 1200, (kind, T, F, n, ids, s)
