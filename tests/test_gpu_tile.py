@@ -195,3 +195,14 @@ def test_lanes_many_trees(kind, size, T, K, ld, n):
     X = np.random.Generator(np.random.PCG64(n)).standard_normal((n, 12)).astype(np.float32)
     strategy = "ptt" if kind == "perfect" else "tt"
     _both(m, X, strategy, "lanes", f"lanes {kind} T{T} K{K} ld{ld} n{n}").close()
+
+
+@pytest.mark.parametrize("F,K", [(40_952, 1), (40_832, 12)])
+def test_lanes_widest_rows(F, K):
+    """Rows that leave LDS for the four waves' sums and nothing more stay on
+    the trees-across-lanes kernel."""
+    m = _forest("perfect", 8, F, 162, K, seed=K)
+    inner = np.flatnonzero(m["feature"] >= 0)
+    m["feature"][inner] = np.arange(inner.size) % F  # every column is used
+    X = np.random.Generator(np.random.PCG64(F)).standard_normal((9, F)).astype(np.float32)
+    _both(m, X, "ptt", "lanes_kernel<", f"lanes F{F} K{K}").close()
