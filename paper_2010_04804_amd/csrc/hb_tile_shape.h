@@ -69,21 +69,22 @@ constexpr int kTileIdStoreAlign = 4;
 //   * a split of k rounds of workgroups is cheapest with the fewest chunks per
 //     workgroup that k rounds hold, so only those are tried, round by round,
 //     until the rounds' loads alone exceed what is gained;
-//   * a chunk size is left out where its bytes, its walks and T / nt hand-overs
-//     (ragged chunks only add to them) already cost more than the best shape.
+//   * a chunk size is left out where its chunks, or with a split their least
+//     share, already cost more than the best shape.
 // Both leave the result as trying everything gives it (time on one host core: 500
-// depth-8 trees with 2-vectors, 10,000 rows 55 us, now 2.2; 3,500 trees of 31
+// depth-8 trees with 2-vectors, 10,000 rows 55 us, now 2.0; 3,500 trees of 31
 // leaves, 7 classes, 4,000 rows 503, now 3.3).
 inline TileShape best_shape(const TileSpec &t, int64_t n_rows, bool ids, int64_t ws_bytes, int lds_max, int cus) {
   TileShape best;
   const bool rank = t.rank;
-  const int64_t max_parts = ws_bytes / (n_rows * t.n_outputs * 8);
+  const int max_parts = (int)std::min<int64_t>(ws_bytes / (n_rows * t.n_outputs * 8), 1 << 20);
   for (int lg = rank ? 7 : 6; lg <= 10; ++lg) {
     const int R = 1 << lg, G = kTileThreads / R;
     const int64_t buf = ((int64_t)t.n_cols * R * (rank ? 2 : 4) + 15) / 16 * 16;
     const int64_t row_tiles = (n_rows + R - 1) / R;
     const double tiles = (double)row_tiles, rounds = std::ceil(tiles / cus), share = tiles / cus;
-    const bool may_split = ws_bytes && row_tiles < cus;
+    const bool may_split = max_parts > 1 && row_tiles < cus;
+    const int few_tiles = (int)std::min<int64_t>(row_tiles, cus);
     const double ranks = rank ? 0.22 * t.n_thr + 11.0 * t.search_steps * (R / 64) : 0.0;
     const double load = ws_bytes ? 2000.0 + 3.0 * t.n_cols * (R / 64) + ranks : ranks;
     // LDS of a tree's id slots: ids are written for up to 32 trees at a time (a 128-byte line per row)
@@ -94,13 +95,15 @@ inline TileShape best_shape(const TileSpec &t, int64_t n_rows, bool ids, int64_t
       for (int ilp : {1, 2, 3, 4, 8}) {
         const double step = std::max(7.0 + 1.0 / ilp, 260.0 / (16 * ilp));
         const double tree = t.levels * (R / 64) * step + t.tree_bytes / 40.0 + (bufs == 1 ? t.tree_bytes / 64.0 : 0.0);
+        const double hand0 = bufs == 1 ? 2000.0 : 1300.0;
         for (int nt = G * ilp; nt <= nt_max; nt += G * ilp) {
-          const double least = t.n_trees * (tree + (bufs == 1 ? 2000.0 : 1300.0) / nt);
-          const double bound = may_split ? load + std::min(least, share * least + 10000.0) : rounds * (least + load);
+          const int n_chunks = (t.n_trees + nt - 1) / nt;
+          const double chunks = (double)n_chunks, chunk = nt * tree + hand0;
+          // (a split takes at least its share of the walks, or one chunk)
+          const double bound = may_split ? load + std::min(chunks * chunk, std::max(share * chunks, 1.0) * chunk + 10000.0)
+                                         : rounds * (chunks * chunk + load);
           if (best.rows && bound >= best.cost) continue;  // (a shape is taken for 0.1% less, far above rounding)
           ++best.tried;
-          const int n_chunks = (t.n_trees + nt - 1) / nt;
-          const double chunks = (double)n_chunks;
           const int64_t slots = nt * slot, stage = buf + (int64_t)bufs * nt * t.tree_bytes;
           int m = 1;
           while (ids && 2 * m * nt <= 32 && stage + 2 * m * slots <= lds_max) m *= 2;
@@ -109,11 +112,11 @@ inline TileShape best_shape(const TileSpec &t, int64_t n_rows, bool ids, int64_t
           const double hand = 1300.0 + bytes / 40.0 + (bufs == 1 ? 700.0 + bytes / 64.0 : 0.0);
           double cost = rounds * (chunks * (walk + hand) + load);
           int split = 0, parts = 1;
-          if (may_split && max_parts > 1) {
-            const int least_per = (int)((n_chunks + max_parts - 1) / max_parts);
-            for (int64_t k = 1;; ++k) {
-              const int64_t most = k * cus / row_tiles;  // parts that k rounds hold (two at least)
-              const int per = std::max(most > 1 ? (int)((n_chunks + most - 1) / most) : n_chunks, least_per);
+          if (may_split) {
+            const int least_per = (n_chunks + max_parts - 1) / max_parts;
+            for (int k = 1;; ++k) {
+              const int most = k * cus / few_tiles;  // parts that k rounds hold
+              const int per = std::max((n_chunks + most - 1) / most, least_per);
               if (per < n_chunks) {
                 ++best.tried;
                 const int p = (n_chunks + per - 1) / per;
