@@ -608,6 +608,11 @@ int launch_tile(bool perfect, const EnsembleDev &e, const TileDev &tile, const T
     }
   }
   if (!p.rows || (n_rows < (int64_t)kTileMinRowsPerCu * cus && p.parts < 2)) return 1;
+  // Leaf ids of fewer than 16 trees at a time leave as short pieces of lines:
+  // beyond 3M walks a leaf-wise split is then slower than the row-parallel one
+  // (800 trees of 255 leaves, 50 columns, flushes of 6 trees, 6,500 rows: 68
+  // against 55 us; at 3,000 rows, 28 against 42).
+  if (!perfect && leaf_ids && p.parts > 1 && p.nt * p.st_chunks < 16 && n_rows * e.n_trees > 3000000) return 1;
   const TileDev &t = *tp;
   const int km = e.n_outputs == 1 ? 1 : e.n_outputs == 2 ? 2 : 16;
   TileArgs a{};

@@ -206,3 +206,24 @@ def test_lanes_widest_rows(F, K):
     m["feature"][inner] = np.arange(inner.size) % F  # every column is used
     X = np.random.Generator(np.random.PCG64(F)).standard_normal((9, F)).astype(np.float32)
     _both(m, X, "ptt", "lanes_kernel<", f"lanes F{F} K{K}").close()
+
+
+def test_lanes_leafwise_four_trees():
+    """Four leaf-wise trees per lane only where a row has more than 256 lanes."""
+    m = _forest("leafwise", 30, 12, 1200, seed=4)
+    h = hb.compile(m, strategy="tt", device=0)
+    for n, kernel in [(200, "lanes4_kernel<false, 1, false>"), (257, "lanes_kernel<false, 1, false, 1>"),
+                      (512, "lanes_kernel<false, 1, false, 1>")]:
+        assert [p["kernel"] for p in h.plan(n, "tt")] == [kernel]
+    h.close()
+
+
+def test_tile_tree_split_of_narrow_rows():
+    """The leaf-wise tree split goes to the tile kernel on rows wide enough
+    to leave the fast kernel few waves on a CU, or for few walks."""
+    for F, T, n, kernel in [(12, 150, 4_500, "tile_kernel<"), (12, 800, 4_500, "fast_kernel<"),
+                            (28, 800, 16_000, "fast_kernel<"), (60, 800, 4_500, "tile_kernel<")]:
+        h = hb.compile(_forest("leafwise", 31, F, T, seed=F + T), strategy="tt", device=0)
+        plan = [p["kernel"] for p in h.plan(n, "tt", hb.workspace_bytes(h, n, "tt"))]
+        assert plan[0].startswith(kernel), (F, T, n, plan)
+        h.close()
