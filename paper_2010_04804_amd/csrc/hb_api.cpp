@@ -16,6 +16,7 @@
 
 #include "hb.h"
 #include "hb_internal.h"
+#include "hb_tile_shape.h"
 
 namespace {
 
@@ -442,9 +443,9 @@ void build_tile(hb_handle *h, const hb_ensemble_desc *d, const std::vector<Canon
                                                                     : select_strategy(h, kAutoPttSmallBatch + 1);
   const bool ptt = strategy == HB_STRATEGY_PTT;
   if (D < 1 || (!ptt && strategy != HB_STRATEGY_TT) || n_cols > hb::kTileMaxCols) return;
-  const size_t padded = (size_t)T + hb::kTilePadTrees;
   if (!ptt) {
     const size_t n_pad = h->tt_n_pad, words = n_pad * 2;
+    const size_t padded = (size_t)T + hb::tile_pad_trees((int)std::min<size_t>(words * 4, hb::kTileChunkMax));
     if (n_pad > 8190 || padded * n_pad * ld * 4 >> 32) return;
     h->tile_leafv.assign(padded * n_pad * ld, 0.0f);
     std::copy(h->tt_leaf_value.begin(), h->tt_leaf_value.end(), h->tile_leafv.begin());
@@ -462,8 +463,8 @@ void build_tile(hb_handle *h, const hb_ensemble_desc *d, const std::vector<Canon
     h->tile_strategy = strategy;
     return;
   }
-  const size_t S = (size_t)1 << D;
-  if (padded * S * ld * 4 >> 32) return;
+  const size_t S = (size_t)1 << D, words = std::max<size_t>(2 * S, 4), rwords = std::max<size_t>(S, 4);
+  if (((size_t)T + hb::kTileChunkTrees) * S * ld * 4 >> 32) return;
   // each column's sorted distinct thresholds, and each node's bound: its
   // threshold's place among them plus one
   bool rank = D >= 11 || n_cols >= 48;
@@ -506,10 +507,10 @@ void build_tile(hb_handle *h, const hb_ensemble_desc *d, const std::vector<Canon
   }
   // (of 32 KiB fp32 trees LDS holds two beside the narrowest rows)
   const bool fp32 = !rank || D < 12;
-  const size_t words = std::max<size_t>(2 * S, 4), rwords = std::max<size_t>(S, 4);
-  if (fp32) h->tile_recs.assign(padded * words, 0u);
-  if (rank) h->rank_recs.assign(padded * rwords, 0u);
-  h->tile_leafv.assign(padded * S * ld, 0.0f);
+  const size_t pad = hb::tile_pad_trees((int)(words * 4)), rpad = hb::tile_pad_trees((int)(rwords * 4));
+  if (fp32) h->tile_recs.assign((T + pad) * words, 0u);
+  if (rank) h->rank_recs.assign((T + rpad) * rwords, 0u);
+  h->tile_leafv.assign((T + std::max(pad, rpad)) * S * ld, 0.0f);
   std::vector<int32_t> at(S);  // canonical node at each path of the present level
   std::vector<uint32_t> entry;
   for (int32_t t = 0; t < T; ++t) {
@@ -892,7 +893,7 @@ int compile_impl(const hb_ensemble_desc *d, int hint, int device, hb_handle **ou
   I.table_bytes[HB_STRATEGY_GEMM] =
       (int64_t)(h->gemm_node.size() * 4 + h->gemm_shape.size() * 4 + h->gemm_ct.size() +
                 h->gemm_bias.size() * 4 + h->gemm_leaf_value.size() * 4 + h->gemm_leaf_id.size() * 4);
-  h->tree_class.assign(T + hb::kTilePadTrees, 0);  // (the tile kernel reads past the last tree)
+  h->tree_class.assign(T + hb::kTileChunkTrees, 0);  // (the tile kernel reads past the last tree)
   if (d->leaf_dim == 1 && d->tree_class)
     for (int32_t t = 0; t < T; ++t) h->tree_class[t] = d->tree_class[t];
   if (d->base_score) {

@@ -132,7 +132,7 @@ constexpr int leaf_pk_words(int leaf_dim) {
 }
 
 // Tables of the tile kernel (hb_tile.hip), one block of tree_bytes per tree,
-// the tree count padded by kTilePadTrees trees whose walks stay in bounds and
+// the tree count padded by tile_pad_trees() trees whose walks stay in bounds and
 // whose leaf values are zero.
 //   PTT, fp32 tile: {threshold bits, feature} at place 2^l + path of level l,
 //     the path's first decision in its lowest bit (a step adds 2^l, and 2^l
@@ -143,7 +143,6 @@ constexpr int leaf_pk_words(int leaf_dim) {
 // distinct thresholds t (thr[thr_off[c] .. thr_off[c + 1])) with not (x < t),
 // in 16 bits; a record's bound is one more than its threshold's place, so
 // x < t holds exactly when rank < bound (bound 0: never).
-constexpr int kTilePadTrees = 64;
 constexpr int kTileMaxCols = 512;  // wider tiles hold fewer than 64 rows of a CU
 struct TileDev {
   const uint4 *recs = nullptr;

@@ -26,6 +26,7 @@ void shape(int n_trees, int n_cols, int n_outputs, int levels, int tree_bytes, i
 int flush_tree(int k, int st) { return hb::tile_flush_tree(k, st); }
 int slot_stride(int rows) { return (int)hb::tile_slot_stride(rows); }
 int store_align() { return hb::kTileIdStoreAlign; }
+int pad_trees(int tree_bytes) { return hb::tile_pad_trees(tree_bytes); }
 }
 """
 FIELDS = ["rows", "split", "parts", "nt", "ilp", "bufs", "st_chunks", "buf_off", "stage_off", "lds", "tried"]
@@ -150,3 +151,14 @@ def test_search_finds_the_shape_and_stays_short(lib):
                                                 (1025, 2000, 4000, 8000, 16_384, 1_000_000), (False, True)):
         s = best(lib, kind, T, F, 1, n, ids, (1 << 30) if n <= 16_384 else 0)
         assert s["tried"] <= 1200, (kind, T, F, n, ids, s)
+
+
+def test_chunks_stay_inside_the_padded_tables(lib):
+    """The tables hold tile_pad_trees trees past the last one: the last chunk of
+    every shape ends inside them."""
+    for kind, T, F, K, n, ws in CASES:
+        for ids in (False, True):
+            s = best(lib, kind, T, F, K, n, ids, ws)
+            if s["rows"]:
+                assert -(-T // s["nt"]) * s["nt"] <= T + lib.pad_trees(TREES[kind][1]), (kind, T, F, K, n, ids, s)
+    assert [lib.pad_trees(b) for b in (16, 1024, 1040, 32768, 65520, 65536)] == [64, 64, 63, 2, 1, 1]
