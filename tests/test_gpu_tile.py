@@ -227,3 +227,16 @@ def test_tile_tree_split_of_narrow_rows():
         plan = [p["kernel"] for p in h.plan(n, "tt", hb.workspace_bytes(h, n, "tt"))]
         assert plan[0].startswith(kernel), (F, T, n, plan)
         h.close()
+
+
+@pytest.mark.parametrize("D,K", [(9, 1), (10, 1), (9, 3), (10, 12)])
+def test_tile_tables_left_out(D, K):
+    """Scalar leaves of depth 9 or 10 on at most 64 columns have no tile
+    tables: the fast kernel holds every batch of them."""
+    m = _forest("perfect", D, 64, 13, K, seed=D)
+    h = hb.compile(m, strategy="ptt", device=0)
+    for n in (2_000, 16_000, 50_000, 70_000, 300_000):
+        for ws in (0, hb.workspace_bytes(h, n, "ptt")):
+            plan = [p["kernel"] for p in h.plan(n, "ptt", ws)]
+            assert plan[0].startswith(("fast_kernel<", "lanes_kernel<")), (D, K, n, ws, plan)
+    h.close()
