@@ -297,15 +297,16 @@ def _gemm_512_model(kind):
 
 
 @pytest.mark.parametrize("kind,n,kernel", [
-    ("cfg2", 65_536, "gemm_pipe_kernel<0, 512>"),
-    ("two_class", 40_000, "gemm_pipe_kernel<1, 512>"),
+    ("cfg2", 65_536, "gemm_block_kernel<0>"),
+    ("two_class", 40_000, "gemm_block_kernel<1>"),
     ("depth7", 40_001, "gemm_kernel<2, true, true, 0, 512, false>"),
     ("depth6", 33_000, "gemm_kernel<1, true, true, 0, 512, false>"),
     ("depth7_vec", 32_768, "gemm_kernel<2, true, true, 2, 512, false>"),
 ])
 def test_gemm_512_row_workgroups(kind, n, kernel):
-    """GEMM with 512-row workgroups (Algorithm 1, Table 3): every row's
-    scores and leaf ids against the oracle. The launch plan the library
+    """GEMM with 512-thread workgroups (Algorithm 1, Table 3): every row's
+    scores and leaf ids against the oracle; perfect trees of depth 8 take the
+    block kernel. The launch plan the library
     reports names the kernel each case is meant to reach, the headline
     workload's included (the one its GEMM throughput is measured on)."""
     m = _gemm_512_model(kind)
@@ -318,6 +319,40 @@ def test_gemm_512_row_workgroups(kind, n, kernel):
     say("gemm 512-row", kind, n, kernel)
     scores, ids = run(h, X, "gemm", workspace=False)
     check(m, X, scores, ids, f"gemm512 {kind}/{n}")
+
+
+@pytest.mark.parametrize("kind,T,n", [("scalar", 1, 32_768), ("scalar", 7, 33_001), ("classes", 6, 32_769),
+                                      ("classes16", 17, 40_001), ("vector", 5, 32_899)])
+def test_gemm_pipe_kernel(kind, T, n):
+    """Forests whose trees share one shape of 255 leaves that is not perfect
+    (the last two leaves of depth 8 are one of depth 7) take the pipelined
+    kernel of the dense product: ragged last workgroups, one tree, one output,
+    classes and vector leaves, with ties, NaN and infinities in the rows."""
+    rng = np.random.Generator(np.random.PCG64(T + n))
+    K = {"scalar": 1, "classes": 3, "classes16": 16, "vector": 3}[kind]
+    ld = K if kind == "vector" else 1
+    m = synth.perfect_forest(rng, T, 8, 24, lambda r, f: r.standard_normal(f.size),
+                             lambda r, k: r.normal(0.0, 0.05, k * ld), leaf_dim=ld)
+    for key in ("feature", "threshold", "left", "right", "leaf_value"):  # heap order: drop nodes 509 and 510
+        a = np.asarray(m[key]).reshape(T, 511, -1)[:, :509].copy()
+        if key != "threshold":
+            a[:, 254] = rng.normal(0.0, 0.05, a[:, 254].shape) if key == "leaf_value" else -1
+        m[key] = a.reshape(-1)
+    m.update(tree_node_offset=np.arange(T + 1, dtype=np.int64) * 509, n_outputs=K,
+             tree_class=(np.arange(T) % K).astype(np.int32) if kind.startswith("classes") else None,
+             aggregation="mean" if ld > 1 else "sum", transform="softmax" if kind.startswith("classes") else "none",
+             base_score=np.linspace(-1, 1, K).astype(np.float32))
+    m = synth.permute_nodes(m, T)
+    h = hb.compile(m, device=0)
+    mode = {"scalar": 0, "vector": 2}.get(kind, 1)
+    assert [p["kernel"] for p in h.plan(n, "gemm")] == [f"gemm_pipe_kernel<{mode}, 512>"]
+    X = np.ascontiguousarray(pins.tricky_rows(rng, m, n))
+    say("gemm pipe", kind, T, n)
+    scores, ids = run(h, X, "gemm", workspace=False)
+    check(m, X, scores, ids, f"gemm pipe {kind}/{T}/{n}")
+    scores, _ = run(h, X, "gemm", leaves=False, workspace=False)
+    check(m, X, scores, None, f"gemm pipe {kind}/{T}/{n} scores only")
+    h.close()
 
 
 def _vector_forest(n_features, n_trees, depth, seed):

@@ -182,7 +182,7 @@ def test_gemm_block_kernel(T, K, ld, n):
     X[rng.random(X.shape) < 0.02] = np.nan
     inner = rng.choice(np.flatnonzero(m["feature"] >= 0), 500)
     X[rng.integers(0, n, 500), m["feature"][inner]] = m["threshold"][inner]
-    _both(m, X, "gemm", "gemm_pipe_kernel<", f"gemm block T{T} K{K} ld{ld} n{n}").close()
+    _both(m, X, "gemm", "gemm_block_kernel<", f"gemm block T{T} K{K} ld{ld} n{n}").close()
 
 
 @pytest.mark.parametrize("kind,size", [("perfect", 5), ("leafwise", 30)])
