@@ -29,10 +29,10 @@ HBM_PEAK = 8.0e12   # B/s, MI355X HBM3E
 INT8_PEAK = 5.0e15  # dense int8 MFMA ops/s, MI355X
 
 
-def kernel_label(h, strat, n, ws_bytes=0):
+def kernel_label(h, strat, n, ws_bytes, leaves):
     """The kernels a call of n rows launches, as the library's own launch
-    plan reports them (hb_plan): "name grid=(x,y) block=b" per launch."""
-    return "; ".join(f"{p['kernel']} grid={p['grid']} block={p['block']}" for p in h.plan(n, strat, ws_bytes))
+    plan reports them (hb_plan_ids): "name grid=(x,y) block=b" per launch."""
+    return "; ".join(f"{p['kernel']} grid={p['grid']} block={p['block']}" for p in h.plan(n, strat, ws_bytes, leaves))
 
 
 PROFILES = os.path.join(ROOT, "profiles")
@@ -416,6 +416,7 @@ def run_configs():
                 torch.cuda.synchronize()
                 probe = _event_ms(stream, fn, 1)
                 ms = _event_ms(stream, fn, int(min(20, max(2, 300.0 / max(probe, 1e-3)))))
+                kernel = kernel_label(h, s, n, 0, leaves)
                 if s == "gemm":
                     frac = gemm_ops(model, n) / (ms * 1e-3) / INT8_PEAK
                 else:
@@ -424,7 +425,7 @@ def run_configs():
                                   "strategy": s, "auto": s == auto, "leaf_ids": leaves,
                                   "ms": round(ms, 4), "rows_per_s": n / (ms * 1e-3),
                                   "bound": "mfma" if s == "gemm" else "hbm", "frac": frac,
-                                  "kernel": kernel_label(h, s, n)}), flush=True)
+                                  "kernel": kernel}), flush=True)
         del X, scores, ids
         h.close()
         torch.cuda.empty_cache()
@@ -533,12 +534,13 @@ def main():
     mfma_measured = mfma_peak_measured()
 
     def roofline(strat, ms):
+        kernel = kernel_label(h, strat, n, ws[strat][1], leaves)
         if strat == "gemm":
             ops = gemm_ops(model, n)
             achieved = ops / (ms * 1e-3)
             r = {"bound": "mfma", "achieved": achieved / 1e12, "peak": INT8_PEAK / 1e12,
                  "unit": "TOP/s", "frac": achieved / INT8_PEAK, "traffic": None,
-                 "kernel": kernel_label(h, strat, n, ws[strat][1]), "avg_launch_ms": ms, "ops_per_launch": ops}
+                 "kernel": kernel, "avg_launch_ms": ms, "ops_per_launch": ops}
             if mfma_measured:
                 r["peak_measured"] = mfma_measured / 1e12
                 r["frac_of_measured"] = achieved / mfma_measured
@@ -547,7 +549,7 @@ def main():
         achieved = b / (ms * 1e-3)
         return {"bound": "hbm", "achieved": achieved / 1e9, "peak": HBM_PEAK / 1e9, "unit": "GB/s",
                 "frac": achieved / HBM_PEAK, "traffic": recorded_traffic(cfg, strat, n, leaves),
-                "kernel": kernel_label(h, strat, n, ws[strat][1]), "avg_launch_ms": ms, "bytes_per_launch": b}
+                "kernel": kernel, "avg_launch_ms": ms, "bytes_per_launch": b}
 
     print(f"[bench] config {cfg}: {n} rows, strategy {strategy}, leaf ids {leaves}", flush=True)
     t_wall = time.perf_counter()

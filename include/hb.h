@@ -290,9 +290,9 @@ HB_API int hb_table(const hb_handle *h, int strategy, const char *name, const vo
 
 /*
  * Dry run of hb_predict_ws: writes into buf (NUL-terminated, at most
- * buf_bytes bytes including the NUL) the kernels a call with this batch size,
- * strategy and workspace size would launch, in launch order, separated by
- * "; ", each as "name grid=(x,y) block=b lds=bytes" with name the kernel
+ * buf_bytes bytes including the NUL) the kernels a call without leaf ids (leaf_ids
+ * NULL) with this batch size, strategy and workspace size would launch, in
+ * launch order, separated by "; ", each as "name grid=(x,y) block=b lds=bytes" with name the kernel
  * template instantiation as a profiler prints it. Launches nothing and needs
  * no buffers; the handle must be a device handle. Errors: those of
  * hb_predict_ws, HB_ERR_INVALID_ARG for a NULL or too small buf. This
@@ -300,6 +300,12 @@ HB_API int hb_table(const hb_handle *h, int strategy, const char *name, const vo
  */
 HB_API int hb_plan(const hb_handle *h, int64_t n_rows, int strategy, int64_t workspace_bytes, char *buf,
                    int64_t buf_bytes);
+
+/* hb_plan for a call that asks for leaf ids (leaf_ids != 0) or not: the kernel
+ * may depend on it, since ids are written in whole lines by some kernels and
+ * in pieces by others. */
+HB_API int hb_plan_ids(const hb_handle *h, int64_t n_rows, int strategy, int64_t workspace_bytes, int leaf_ids,
+                       char *buf, int64_t buf_bytes);
 
 /* Synchronise the handle's device and free everything it owns. NULL is a no-op. */
 HB_API void hb_destroy(hb_handle *h);

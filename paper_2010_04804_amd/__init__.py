@@ -3,7 +3,7 @@
 This module only marshals arguments into the C-ABI declared in
 ``include/hb.h`` (``hb_compile``, ``hb_predict``, ``hb_predict_ws``,
 ``hb_predict_scratch``, ``hb_workspace_bytes``, ``hb_query``, ``hb_table``, ``hb_select_strategy``,
-``hb_plan``, ``hb_destroy``, ``hb_last_error``). Every step of
+``hb_plan``, ``hb_plan_ids``, ``hb_destroy``, ``hb_last_error``). Every step of
 scoring runs in the library's HIP kernels; PyTorch only supplies device
 memory and the current stream. If ``libhb.so`` has not been built, importing
 works but every call raises.
@@ -93,6 +93,9 @@ def load_library(path: str = LIB_PATH):
                              ctypes.POINTER(ctypes.c_int64)]
     lib.hb_plan.restype = ctypes.c_int
     lib.hb_plan.argtypes = [_P, ctypes.c_int64, ctypes.c_int, ctypes.c_int64, ctypes.c_char_p, ctypes.c_int64]
+    lib.hb_plan_ids.restype = ctypes.c_int
+    lib.hb_plan_ids.argtypes = [_P, ctypes.c_int64, ctypes.c_int, ctypes.c_int64, ctypes.c_int, ctypes.c_char_p,
+                                ctypes.c_int64]
     lib.hb_destroy.restype = None
     lib.hb_destroy.argtypes = [_P]
     lib.hb_last_error.restype = ctypes.c_char_p
@@ -149,12 +152,13 @@ class Handle:
             _check(rc)
         return STRATEGY_NAME[rc]
 
-    def plan(self, n_rows: int, strategy="auto", workspace_bytes: int = 0) -> list:
-        """The kernels hb_predict_ws would launch for this batch, scores only (hb_plan):
-        one dict per launch with the kernel's template name, grid, block and
-        dynamic LDS bytes."""
+    def plan(self, n_rows: int, strategy="auto", workspace_bytes: int = 0, leaves: bool = False) -> list:
+        """The kernels hb_predict_ws would launch for this batch, with leaf ids
+        or scores only (hb_plan_ids): one dict per launch with the kernel's
+        template name, grid, block and dynamic LDS bytes."""
         buf = ctypes.create_string_buffer(4096)
-        _check(load_library().hb_plan(self.ptr, int(n_rows), _strategy(strategy), int(workspace_bytes), buf, 4096))
+        _check(load_library().hb_plan_ids(self.ptr, int(n_rows), _strategy(strategy), int(workspace_bytes), int(leaves),
+                                          buf, 4096))
         out = []
         for part in filter(None, buf.value.decode().split("; ")):
             name, rest = part.split(" grid=(")

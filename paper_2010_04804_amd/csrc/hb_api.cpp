@@ -1226,14 +1226,20 @@ int hb_predict_ws(hb_handle *h, const float *X, int64_t n_rows, float *scores, i
 }
 
 int hb_plan(const hb_handle *h, int64_t n_rows, int strategy, int64_t workspace_bytes, char *buf, int64_t buf_bytes) {
+  return hb_plan_ids(h, n_rows, strategy, workspace_bytes, 0, buf, buf_bytes);
+}
+
+int hb_plan_ids(const hb_handle *h, int64_t n_rows, int strategy, int64_t workspace_bytes, int leaf_ids, char *buf,
+                int64_t buf_bytes) {
   if (!buf || buf_bytes < 1) return fail(HB_ERR_INVALID_ARG, "buf is NULL or empty");
   buf[0] = '\0';
   if (workspace_bytes < 0) return fail(HB_ERR_INVALID_ARG, "workspace_bytes < 0");
   std::string plan;
-  // the dry run reads the workspace pointer only to test it for NULL and alignment
-  void *ws = workspace_bytes > 0 ? reinterpret_cast<void *>(uintptr_t(256)) : nullptr;
-  const int rc = predict_impl(const_cast<hb_handle *>(h), nullptr, n_rows, nullptr, nullptr, strategy, nullptr, ws,
-                              workspace_bytes, &plan);
+  // the dry run reads these pointers only to test them for NULL and alignment
+  void *some = reinterpret_cast<void *>(uintptr_t(256));
+  const int rc = predict_impl(const_cast<hb_handle *>(h), nullptr, n_rows, nullptr,
+                              leaf_ids ? static_cast<int32_t *>(some) : nullptr, strategy, nullptr,
+                              workspace_bytes > 0 ? some : nullptr, workspace_bytes, &plan);
   if (rc) return rc;
   if ((int64_t)plan.size() >= buf_bytes) return fail(HB_ERR_INVALID_ARG, "buf too small for the plan");
   std::memcpy(buf, plan.c_str(), plan.size() + 1);

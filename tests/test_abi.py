@@ -50,6 +50,18 @@ def test_plan_needs_a_device_handle():
     assert e.value.code == -1 and "host-only" in str(e.value)
 
 
+def test_bench_reports_the_call_it_times():
+    """bench.py plans a call as it makes it, with or without leaf ids."""
+    import bench
+
+    class Planned:
+        def plan(self, n_rows, strategy, workspace_bytes, leaves):
+            return [{"kernel": f"k{n_rows}{strategy}{workspace_bytes}{leaves}", "grid": (1, 1), "block": 64}]
+
+    assert [bench.kernel_label(Planned(), "tt", 5, 8, leaves).split()[0] for leaves in (True, False)] == ["k5tt8True",
+                                                                                                            "k5tt8False"]
+
+
 def test_host_only_handle_cannot_predict():
     h = hb.compile(synth.make_model(1), device=-1)
     with pytest.raises(hb.HBError) as e:

@@ -36,13 +36,16 @@ def _forest(kind, size, F, T, K=1, ld=1, seed=0, spread=1, base=False):
     return m
 
 
-def _both(m, X, strategy, expect, label):
-    """Scores with and without leaf ids, on the kernel the plan names (that of
-    a call without leaf ids)."""
+def _both(m, X, strategy, expect, label, expect_ids=None):
+    """Scores with leaf ids (and a workspace) and without either, each on the
+    kernel its plan names."""
     h = hb.compile(m, strategy=strategy, device=0)
-    plan = [p["kernel"] for p in h.plan(X.shape[0], strategy)]
-    say(label, plan)
+    n = X.shape[0]
+    plan = [p["kernel"] for p in h.plan(n, strategy)]
+    plan_ids = [p["kernel"] for p in h.plan(n, strategy, hb.workspace_bytes(h, n, strategy), leaves=True)]
+    say(label, plan, plan_ids)
     assert plan[0].startswith(expect), plan
+    assert plan_ids[0].startswith(expect_ids or expect), plan_ids
     s, ids = run(h, X, strategy)
     check(m, X, s, ids, label)
     s, none = run(h, X, strategy, leaves=False, workspace=False)
@@ -51,7 +54,10 @@ def _both(m, X, strategy, expect, label):
     return h
 
 
-# kind, depth or leaves, columns, trees, classes, leaf values, rows past ROWS, column spread, strategy, kernel
+# kind, depth or leaves, columns, trees, classes, leaf values, rows past ROWS, column spread, strategy, kernel;
+# with leaf ids the fast kernel takes the cases of few columns and perfect trees (FAST_IDS)
+FAST_IDS = {(1, 300): "fast_kernel<3, 1, 2, 512", (5, 28): "fast_kernel<0, 5, 2, 512",
+            (7, 40): "fast_kernel<3, 7, 16, 512", (8, 54): "fast_kernel<3, 8, 16, 512"}
 CASES = [
     ("perfect", 8, 130, 33, 1, 1, 0, 1, "ptt", "tile_kernel<true, false, 1, false"),     # a chunk and a tree
     ("perfect", 7, 203, 5, 1, 1, 1, 1, "ptt", "tile_kernel<true, false, 1, false"),      # fewer trees than a chunk
@@ -75,7 +81,8 @@ def test_tile_kernel(kind, size, F, T, K, ld, extra, spread, strategy, expect):
     m = _forest(kind, size, F, T, K, ld, seed=size + F + T, spread=spread, base=K > 1)
     n = ROWS + extra
     X = np.random.Generator(np.random.PCG64(n + F)).standard_normal((n, F * spread)).astype(np.float32)
-    _both(m, X, strategy, expect, f"tile {kind}{size} F{F}x{spread} T{T} K{K} ld{ld} n{n}").close()
+    _both(m, X, strategy, expect, f"tile {kind}{size} F{F}x{spread} T{T} K{K} ld{ld} n{n}",
+          FAST_IDS.get((size, F))).close()
 
 
 @pytest.mark.parametrize("kind,size,F,T,strategy", [
@@ -134,9 +141,10 @@ def test_tile_tree_split(kind, size, F, T, K, ld, n):
     m = _forest(kind, size, F, T, K, ld, seed=size + n, base=True)
     strategy = "ptt" if kind == "perfect" else "tt"
     h = hb.compile(m, strategy=strategy, device=0)
-    plan = [p["kernel"] for p in h.plan(n, strategy, hb.workspace_bytes(h, n, strategy))]
-    say("tile split", kind, size, F, T, K, ld, n, plan)
-    assert plan[0].startswith("tile_kernel<") and plan[1].startswith("split_finish"), plan
+    for leaves in (False, True):
+        plan = [p["kernel"] for p in h.plan(n, strategy, hb.workspace_bytes(h, n, strategy), leaves)]
+        say("tile split", kind, size, F, T, K, ld, n, leaves, plan)
+        assert plan[0].startswith("tile_kernel<") and plan[1].startswith("split_finish"), plan
     X = np.random.Generator(np.random.PCG64(n)).standard_normal((n, F)).astype(np.float32)
     s, ids = run(h, X, strategy)
     check(m, X, s, ids, f"tile split {kind}{size} T{T} n{n}")
@@ -147,7 +155,7 @@ def test_tile_tree_split(kind, size, F, T, K, ld, n):
 
 @pytest.mark.parametrize("kind,size,F,T,ld,n,workspace", [
     ("perfect", 9, 60, 100, 2, 50_003, False),      # chunks of 6 trees, one per flush
-    ("leafwise", 256, 10, 800, 1, 8_000, True)])    # tree split in parts of 27 trees, chunks of 9
+    ("perfect", 8, 60, 400, 2, 8_000, True)])       # tree split in parts of 30 trees, chunks of 6
 def test_tile_leaf_ids_start_at_any_tree(kind, size, F, T, ld, n, workspace):
     """Leaf-id rows 16-byte aligned (T a multiple of four) and flushes that
     start at no multiple of four trees and end on a lane's first or second
@@ -158,7 +166,9 @@ def test_tile_leaf_ids_start_at_any_tree(kind, size, F, T, ld, n, workspace):
     X = np.random.Generator(np.random.PCG64(n)).standard_normal((n, F)).astype(np.float32)
     Xd = torch.from_numpy(X).cuda()
     nws = hb.workspace_bytes(h, n, strategy) if workspace else 0
-    say("tile ids", kind, size, F, T, ld, n, nws)
+    plan = [p["kernel"] for p in h.plan(n, strategy, nws, leaves=True)]
+    say("tile ids", kind, size, F, T, ld, n, nws, plan)
+    assert plan[0].startswith("tile_kernel<") and (len(plan) == 2) == workspace, plan
     buf = torch.full((n * T + 8,), -7, dtype=torch.int32, device="cuda")
     sc = torch.empty((n, max(1, ld)), dtype=torch.float32, device="cuda")
     ws = torch.empty(max(nws, 8), dtype=torch.uint8, device="cuda")
@@ -220,12 +230,16 @@ def test_lanes_leafwise_four_trees():
 
 def test_tile_tree_split_of_narrow_rows():
     """The leaf-wise tree split goes to the tile kernel on rows wide enough
-    to leave the fast kernel few waves on a CU, or for few walks."""
-    for F, T, n, kernel in [(12, 150, 4_500, "tile_kernel<"), (12, 800, 4_500, "fast_kernel<"),
-                            (28, 800, 16_000, "fast_kernel<"), (60, 800, 4_500, "tile_kernel<")]:
-        h = hb.compile(_forest("leafwise", 31, F, T, seed=F + T), strategy="tt", device=0)
-        plan = [p["kernel"] for p in h.plan(n, "tt", hb.workspace_bytes(h, n, "tt"))]
-        assert plan[0].startswith(kernel), (F, T, n, plan)
+    to leave the fast kernel few waves on a CU, or for few walks; with leaf
+    ids, beyond 3M walks, only in flushes of 16 trees."""
+    tile, fast = "tile_kernel<", "fast_kernel<"
+    for leaves_, F, T, n, kernel, kernel_ids in [
+            (31, 12, 150, 4_500, tile, tile), (31, 12, 800, 4_500, fast, fast), (31, 28, 800, 16_000, fast, fast),
+            (31, 60, 800, 4_500, tile, fast), (255, 50, 800, 3_000, tile, tile), (255, 50, 800, 6_500, tile, fast)]:
+        h = hb.compile(_forest("leafwise", leaves_, F, T, seed=F + T), strategy="tt", device=0)
+        for ids, expect in ((False, kernel), (True, kernel_ids)):
+            plan = [p["kernel"] for p in h.plan(n, "tt", hb.workspace_bytes(h, n, "tt"), ids)]
+            assert plan[0].startswith(expect), (leaves_, F, T, n, ids, plan)
         h.close()
 
 
