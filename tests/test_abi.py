@@ -51,7 +51,8 @@ def test_plan_needs_a_device_handle():
 
 
 def test_bench_reports_the_call_it_times():
-    """bench.py plans a call as it makes it, with or without leaf ids."""
+    """bench.py plans a call as it makes it, with or without leaf ids, and
+    counts for the block GEMM kernel the operations it executes."""
     import bench
 
     class Planned:
@@ -60,6 +61,10 @@ def test_bench_reports_the_call_it_times():
 
     assert [bench.kernel_label(Planned(), "tt", 5, 8, leaves).split()[0] for leaves in (True, False)] == ["k5tt8True",
                                                                                                             "k5tt8False"]
+    m = synth.perfect_forest(np.random.Generator(np.random.PCG64(1)), 3, 8, 4, lambda r, f: r.standard_normal(f.size),
+                             lambda r, k: r.standard_normal(k))
+    assert bench.gemm_executed_ops(m, 10, "gemm_pipe_kernel<0, 512>") == bench.gemm_ops(m, 10) == 2 * 10 * 3 * 255 * 256
+    assert bench.gemm_executed_ops(m, 10, "gemm_block_kernel<0> grid=(1, 1)") == 2 * 10 * 3 * 64 * 256
 
 
 def test_host_only_handle_cannot_predict():
