@@ -254,3 +254,64 @@ def test_tile_tables_left_out(D, K):
             plan = [p["kernel"] for p in h.plan(n, "ptt", ws)]
             assert plan[0].startswith(("fast_kernel<", "lanes_kernel<")), (D, K, n, ws, plan)
     h.close()
+
+
+def _deep_columns(T, F, counts, draw):
+    """Perfect trees of depth 12 whose decision nodes test column c counts[c]
+    times (the columns of the rest drawn from those past counts), thresholds
+    from draw(rng, column, number)."""
+    rng = np.random.Generator(np.random.PCG64(T))
+    m = _forest("perfect", 12, F, T, seed=T)
+    inner = rng.permutation(np.flatnonzero(m["feature"] >= 0))
+    f = rng.integers(len(counts), max(F - 3, len(counts) + 1), inner.size)  # (the last three columns: no node)
+    f[:sum(counts)] = np.repeat(np.arange(len(counts)), counts)
+    m["feature"][inner] = f
+    m["threshold"] = m["threshold"].copy()
+    for c in range(F):
+        at = inner[f == c]
+        m["threshold"][at] = draw(rng, c, at.size)
+    return m
+
+
+@pytest.mark.parametrize("F,n", [(16, ROWS + 37), (16, 3_001), (180, ROWS + 5)])
+def test_tile_ranks_of_sampled_columns(F, n):
+    """Columns with more distinct thresholds (58,001 and 36,003) than fit in
+    LDS: every second (16 columns) or fourth (180) passes through it and the
+    last steps of a search are taken in global memory. Short columns and columns that no node
+    tests lie beside them; rows hold ties with any of the thresholds, their
+    neighbours, infinities and NaN."""
+    def draw(rng, c, k):
+        t = rng.standard_normal(k).astype(np.float32)
+        if k > 8:
+            t[:4] = [np.inf, -np.inf, -0.0, 0.0]
+        return t
+
+    m = _deep_columns(40, F, (58_001, 36_003), draw)
+    rng = np.random.Generator(np.random.PCG64(n))
+    X = rng.standard_normal((n, F)).astype(np.float32)
+    for c in range(F - 3):
+        t = np.unique(m["threshold"][m["feature"] == c])
+        assert c > 1 or t.size > 35_000
+        pick = rng.choice(t, n)
+        near = np.nextafter(pick, rng.choice(np.float32([np.inf, -np.inf]), n))
+        X[:, c] = np.select([rng.random(n) < 0.3, rng.random(n) < 0.6], [pick, near], X[:, c])
+        X[rng.random(n) < 0.02, c] = np.nan
+        X[rng.random(n) < 0.02, c] = rng.choice([np.inf, -np.inf])
+    _both(m, X, "ptt", "tile_kernel<true, true, 1, false" if n >= ROWS else "lanes", f"tile sampled ranks F{F} n{n}",
+          "tile_kernel<true, true, 1, false").close()
+
+
+@pytest.mark.parametrize("distinct,ranked", [(65_534, True), (65_535, False)])
+def test_tile_rank_limit(distinct, ranked):
+    """16-bit ranks hold a column of 65,534 distinct thresholds; one more and
+    the model keeps the fp32 tile."""
+    def draw(rng, c, k):
+        return rng.permutation(np.arange(k)).astype(np.float32) if c == 0 else rng.standard_normal(k)
+
+    m = _deep_columns(17, 5, (distinct,), draw)
+    n = ROWS + 3
+    rng = np.random.Generator(np.random.PCG64(distinct))
+    X = rng.standard_normal((n, 5)).astype(np.float32)
+    X[:, 0] = rng.integers(-2, distinct + 2, n) + rng.choice([0.0, 0.5], n)
+    X[:8, 0] = [-1, 0, distinct - 1, distinct - 2, distinct, np.inf, -np.inf, np.nan]
+    _both(m, X, "ptt", f"tile_kernel<true, {'true' if ranked else 'false'}, 1, false", f"tile rank limit {distinct}").close()
