@@ -143,7 +143,7 @@ constexpr int leaf_pk_words(int leaf_dim) {
 // distinct thresholds t (thr[thr_off[c] .. thr_off[c + 1])) with not (x < t),
 // in 16 bits; a record's bound is one more than its threshold's place, so
 // x < t holds exactly when rank < bound (bound 0: never).
-constexpr int kTileMaxCols = 512;  // wider tiles hold fewer than 64 rows of a CU
+constexpr int kTileMaxCols = 512;  // 64 rows of it take 128 KiB of LDS; wider ones were not measured
 struct TileDev {
   const uint4 *recs = nullptr;
   int32_t tree_bytes = 0;

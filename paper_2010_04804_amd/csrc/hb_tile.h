@@ -5,10 +5,14 @@
 
 namespace hb {
 
-// Smaller batches leave CUs without a workgroup; they keep the other kernels
-// (whose trees a workspace splits).
+// Without a tree split the tile kernel takes batches from this size on: its launch
+// rules were measured from 50,000 rows up. It is no limit of the kernel, which
+// gives every CU a workgroup of 64 rows from 16,384 rows on.
 constexpr int kTileMinRowsPerCu = 192;
-// Batches up to this size may have their trees split by the tile kernel.
+// With a workspace, batches up to this size may have their trees split by the
+// tile kernel (measured from 1,100 to 16,384 rows). The batches between the two
+// keep the kernels they had before the tile kernel; where trees are deeper than
+// 10, that is the general one.
 constexpr int64_t kTileSplitMaxRows = 16384;
 
 // Launches the tile kernel with the fp32 tile's tables, or the rank tile's

@@ -80,8 +80,9 @@ __device__ __forceinline__ uint32_t row_off(uint32_t r) {
 }
 
 // LDS byte address of a record's feature in this lane's column position: one
-// multiply-add of a 16-bit half of the record's word (PTT fp32: the low 24
-// bits) with the column stride.
+// multiply-add of a 16-bit half of the record's word (PTT and TT fp32 records
+// hold the feature in the low half, rank records in the high one) with the
+// column stride, which 16 bits hold too (4 bytes of at most 1,024 rows).
 template <bool HIGH>
 __device__ __forceinline__ uint32_t xaddr16(uint32_t w, uint32_t stride, uint32_t xlane) {
   uint32_t r;
