@@ -810,8 +810,10 @@ int validate_desc(const hb_ensemble_desc *d) {
   return HB_OK;
 }
 
-// Models below this many nodes build the tile kernel's tables in turn: some 30
-// ns a node, against about 50 us for a thread.
+// Models below this many nodes build the tile kernel's tables in turn: the
+// memory that a second thread touches first costs more than it hides (100
+// depth-6 trees, 12,700 nodes: 0.55 ms in turn, 0.71 beside; 500 depth-8 trees,
+// 255,500 nodes, 7.1 and 6.9; 100 depth-12 trees, 819,100 nodes, 16.6 and 14.1).
 constexpr int64_t kTileThreadNodes = 200000;
 
 int compile_impl(const hb_ensemble_desc *d, int hint, int device, hb_handle **out) {
